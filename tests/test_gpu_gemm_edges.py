@@ -116,6 +116,54 @@ def test_operands_at_the_end_of_an_allocation():
                 assert np.array_equal(to_f64(c), a.T @ b), (dt, k, tile)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 7, 8])
+@pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
+@pytest.mark.parametrize("din,dout", [("f32", "f32"), ("bf16", "bf16"), ("bf16", "f32")])
+def test_empty_sum(din, dout, layout, tile):
+    """k = 0 (the weight gradient of an empty batch): C = epilogue(0) bit for bit, in every call that multiplies,
+    whatever the workgroups before have left in LDS."""
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    ta, tb = layout == "TN", layout == "NT"
+    nan = torch.full((512, 512), float("nan"), dtype=tdt[din], device=DEV)
+    scratch = torch.empty(512, 512, dtype=tdt[dout], device=DEV)
+    with T.tuning(gemm_tile=4):
+        T.tfd_matmul(nan, nan, scratch)  # every stage of its workgroups holds NaN
+    for m, n in [(3, 5), (264, 136), (600, 512)]:
+        a = torch.empty((0, m) if ta else (m, 0), dtype=tdt[din], device=DEV)
+        b = torch.empty((n, 0) if tb else (0, n), dtype=tdt[din], device=DEV)
+        kw = dict(transpose_a=ta, transpose_b=tb)
+        bias = torch.linspace(-1.0, 1.0, n, device=DEV)
+        new = lambda dt=dout: torch.full((m, n), float("nan"), dtype=tdt[dt], device=DEV)  # noqa: E731
+        y = bias.to(tdt[dout]).expand(m, n)
+        relu = torch.where(y > 0, y, torch.zeros_like(y))
+        with T.tuning(gemm_tile=tile):
+            for epi, want in [("none", torch.zeros_like(y)), ("bias", y), ("bias_relu", relu)]:
+                c = new()
+                T.tfd_matmul(a, b, c, bias=None if epi == "none" else bias, epilogue=epi, **kw)
+                assert torch.equal(c, want) and not torch.signbit(c[want == 0]).any(), (epi, m, n)
+            if din != dout:
+                continue
+            feats = torch.randn(m, n, device=DEV).to(tdt[din])
+            mask, want_mask = T.new_relu_mask(m, n, DEV), T.new_relu_mask(m, n, DEV)
+            c = new()
+            T.tfd_matmul_relu_mask(a, b, bias, c, mask, **kw)
+            T.tfd_relu_mask(relu.contiguous(), want_mask)
+            assert torch.equal(c, relu) and torch.equal(mask, want_mask), (m, n)
+            for call, arg in [(T.tfd_matmul_relu_grad_bias_add_grad, feats),
+                              (T.tfd_matmul_relu_mask_grad_bias_add_grad, mask)]:
+                bp, db = new(), torch.full((n,), float("nan"), device=DEV)
+                call(a, b, arg, bp, db, **kw)
+                assert not bp.any() and not db.any(), (call, m, n)
+            out, grad, db = new(), new(), torch.full((n,), float("nan"), device=DEV)
+            loss = torch.full((1,), float("nan"), dtype=torch.float64, device=DEV)
+            T.tfd_matmul_l2_loss_grad(a, b, bias, out, feats, grad, loss, db, **kw)
+            want_grad, want_loss = new(), torch.zeros(1, dtype=torch.float64, device=DEV)
+            T.tfd_l2_loss_grad(y.contiguous(), feats, want_grad, want_loss)
+            assert torch.equal(out, y) and torch.equal(grad, want_grad) and torch.equal(loss, want_loss), (m, n)
+            want_db = want_grad.double().sum(0)  # m values in some order
+            assert ((db - want_db).abs() <= 2 * m * 2.0 ** -24 * want_grad.double().abs().sum(0)).all(), (m, n)
+
+
 # gemm_bf16_128.hip takes whole 16-byte units: one of them; one unit below, at
 # and above a tile edge and a k-tile, fewer k-tiles than stages; with two stages
 # (more than 256 tiles); 256 x 128 tiles (10 k-tiles, more than 256 square ones)
