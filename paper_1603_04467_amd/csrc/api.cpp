@@ -139,23 +139,33 @@ int split_plan(const tfd::GemmDesc& d, int64_t* kt_per, size_t* bytes) {
   return s;
 }
 
-// Whether the kernel of this MatMul has the fused epilogues, and its launch.
-bool fused_epilogues(const tfd::GemmDesc& d) { return tfd::gemm_route(d) != tfd::GemmRoute::kOther; }
-hipError_t launch_fused(const tfd::GemmDesc& d, hipStream_t s) {
-  return tfd::gemm_route(d) == tfd::GemmRoute::kBf16Whole256 ? tfd::launch_gemm_bf16_256(d, s)
-                                                             : tfd::launch_gemm_bf16_128(d, s);
-}
-// Tile rows, each with its row of column sums, of a fused MatMul; 0: not fused,
-// also where the sums do not fit into the `need` bytes that the call's workspace
-// has at least (very wide outputs on 128 x 128 tiles).
-int64_t fused_rows(const tfd::GemmDesc& d, size_t need) {
+// How a fused call runs, decided once per call: the tuning knobs that the route
+// reads may change on another thread at any time, and the column sums, the loss
+// partials and the launch must belong to one kernel.
+struct FusedPlan {
+  tfd::GemmRoute route;  // kOther: the separate calls
+  int64_t rows, tiles;   // tile rows, each with its row of column sums; tiles
+};
+FusedPlan fused_plan(const tfd::GemmDesc& d) {
   const tfd::GemmRoute r = tfd::gemm_route(d);
-  if (r == tfd::GemmRoute::kOther) return 0;
-  const int64_t rows = r == tfd::GemmRoute::kBf16Whole256 ? d.m / 256 : tfd::gemm_bf16_128_tile_rows(d);
-  return (size_t)rows * (size_t)d.n * sizeof(float) <= need ? rows : 0;
+  if (r == tfd::GemmRoute::kBf16Whole256) return {r, d.m / 256, (d.m / 256) * (d.n / 256)};
+  if (r == tfd::GemmRoute::kBf16Tiles128) return {r, tfd::gemm_bf16_128_tile_rows(d), tfd::gemm_bf16_128_tiles(d)};
+  return {tfd::GemmRoute::kOther, 0, 0};
 }
-int64_t fused_tiles(const tfd::GemmDesc& d) {
-  return tfd::gemm_route(d) == tfd::GemmRoute::kBf16Whole256 ? (d.m / 256) * (d.n / 256) : tfd::gemm_bf16_128_tiles(d);
+// The same for a call whose column sums (of any fused m > 0) go to `need` bytes
+// of workspace: the separate calls where they do not fit (very wide outputs on
+// 128 x 128 tiles).
+FusedPlan fused_plan(const tfd::GemmDesc& d, size_t need) {
+  if (d.m == 0) return {tfd::GemmRoute::kOther, 0, 0};
+  const FusedPlan p = fused_plan(d);
+  if ((size_t)p.rows * (size_t)d.n * sizeof(float) > need) return {tfd::GemmRoute::kOther, 0, 0};
+  return p;
+}
+bool fused(const FusedPlan& p) { return p.route != tfd::GemmRoute::kOther; }
+hipError_t launch_fused(const FusedPlan& p, const tfd::GemmDesc& d, hipStream_t s) {
+  if (p.route == tfd::GemmRoute::kBf16Whole256) return tfd::launch_gemm_bf16_256(d, s);
+  if (p.route == tfd::GemmRoute::kBf16Tiles128) return tfd::launch_gemm_bf16_128(d, s);
+  return hipErrorInvalidValue;
 }
 
 tfd_status matmul_impl(const char* fn, int transpose_a, int transpose_b, int64_t m, int64_t n, int64_t k,
@@ -468,10 +478,10 @@ tfd_status tfd_matmul_relu_grad_bias_add_grad(int transpose_a, int transpose_b, 
   d.features = features;
   d.ldf = n;
   d.col_partial = static_cast<float*>(workspace);
-  if (const int64_t rows = m > 0 ? fused_rows(d, need) : 0) {
-    hipError_t e = launch_fused(d, st);
+  if (const FusedPlan plan = fused_plan(d, need); fused(plan)) {
+    hipError_t e = launch_fused(plan, d, st);
     if (e != hipSuccess) return hip_status(e, "tfd_matmul_relu_grad_bias_add_grad launch");
-    return hip_status(tfd::launch_colsum_final(static_cast<const float*>(workspace), bias_grad, rows, n, st),
+    return hip_status(tfd::launch_colsum_final(static_cast<const float*>(workspace), bias_grad, plan.rows, n, st),
                       "tfd_matmul_relu_grad_bias_add_grad launch");
   }
   // other shapes: the MatMul writes G into backprops, then ReluGrad and
@@ -550,7 +560,8 @@ tfd_status tfd_matmul_relu_mask(int transpose_a, int transpose_b, int64_t m, int
   d.mask_out = relu_mask;
   d.ldm = ldm;
   hipStream_t s = as_stream(stream);
-  if (fused_epilogues(d)) return hip_status(launch_fused(d, s), "tfd_matmul_relu_mask launch");
+  if (const FusedPlan plan = fused_plan(d); fused(plan))
+    return hip_status(launch_fused(plan, d, s), "tfd_matmul_relu_mask launch");
   // other shapes: the MatMul, then the mask of its stored output
   d.mask_out = nullptr;
   hipError_t e = tfd::launch_gemm(d, s);
@@ -640,10 +651,10 @@ tfd_status tfd_matmul_relu_mask_grad_bias_add_grad(int transpose_a, int transpos
   d.mask_in = relu_mask;
   d.ldm = ldm;
   d.col_partial = static_cast<float*>(workspace);
-  if (const int64_t rows = m > 0 ? fused_rows(d, need) : 0) {
-    hipError_t e = launch_fused(d, st);
+  if (const FusedPlan plan = fused_plan(d, need); fused(plan)) {
+    hipError_t e = launch_fused(plan, d, st);
     if (e != hipSuccess) return hip_status(e, "tfd_matmul_relu_mask_grad_bias_add_grad launch");
-    return hip_status(tfd::launch_colsum_final(static_cast<const float*>(workspace), bias_grad, rows, n, st),
+    return hip_status(tfd::launch_colsum_final(static_cast<const float*>(workspace), bias_grad, plan.rows, n, st),
                       "tfd_matmul_relu_mask_grad_bias_add_grad launch");
   }
   // other shapes: the MatMul writes G into backprops, then ReluGrad (from the
@@ -732,15 +743,15 @@ tfd_status tfd_matmul_l2_loss_grad(int transpose_a, int transpose_b, int64_t m, 
   d.grad = grad;
   // column sums of each tile row, then a sum of squares of each tile; the
   // other shapes' calls need no less on 128 x 128 tiles but for very wide outputs
-  const int64_t rows = m > 0 && target ? fused_rows(d, need) : 0, tiles = rows ? fused_tiles(d) : 0;
-  const size_t sums = (size_t)rows * (size_t)n * sizeof(float);
+  const FusedPlan plan = target ? fused_plan(d, need) : FusedPlan{tfd::GemmRoute::kOther, 0, 0};
+  const size_t sums = (size_t)plan.rows * (size_t)n * sizeof(float);
   d.col_partial = static_cast<float*>(workspace);
   d.loss_partial = reinterpret_cast<double*>(static_cast<char*>(workspace) + sums);
-  if (rows && (reinterpret_cast<uintptr_t>(d.loss_partial) & 7) == 0 && tiles < (1LL << 31) &&
-      sums + (size_t)tiles * sizeof(double) <= need) {
-    hipError_t e = launch_fused(d, st);
-    if (e == hipSuccess) e = tfd::launch_colsum_final(d.col_partial, bias_grad, rows, n, st);
-    if (e == hipSuccess) e = tfd::launch_loss_final(d.loss_partial, (int)tiles, loss, st);
+  if (fused(plan) && (reinterpret_cast<uintptr_t>(d.loss_partial) & 7) == 0 && plan.tiles < (1LL << 31) &&
+      sums + (size_t)plan.tiles * sizeof(double) <= need) {
+    hipError_t e = launch_fused(plan, d, st);
+    if (e == hipSuccess) e = tfd::launch_colsum_final(d.col_partial, bias_grad, plan.rows, n, st);
+    if (e == hipSuccess) e = tfd::launch_loss_final(d.loss_partial, (int)plan.tiles, loss, st);
     return hip_status(e, "tfd_matmul_l2_loss_grad launch");
   }
   // other shapes: the three calls in sequence (they share the workspace in

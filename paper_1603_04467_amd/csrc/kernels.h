@@ -70,10 +70,12 @@ float gemm_bf16_128_us(const GemmDesc& d);
 int64_t gemm_bf16_128_tile_rows(const GemmDesc& d);
 int64_t gemm_bf16_128_tiles(const GemmDesc& d);
 hipError_t launch_gemm_bf16_128(const GemmDesc& d, hipStream_t s);
-// The kernel that a MatMul runs on. It follows from the shape, the types and the
-// alignment alone, so that a fused call computes the plain one's bits: the two
-// 16-bit kernels with the fused epilogues, or launch_gemm's others, which have
-// none.
+// The kernel that a MatMul runs on: the two 16-bit kernels with the fused
+// epilogues, or launch_gemm's others, which have none. It follows from the
+// shape, the types, the alignment and the tuning knobs, so that a fused call
+// computes the plain one's bits under the same knobs. Another thread may set a
+// knob between two calls of this function: a caller asks once and keeps the
+// answer.
 enum class GemmRoute { kOther, kBf16Whole256, kBf16Tiles128 };
 GemmRoute gemm_route(const GemmDesc& d);
 // Number of k splits worth using for a whole-tile 16-bit problem on `cus`

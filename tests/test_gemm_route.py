@@ -1,0 +1,101 @@
+"""Which kernel a MatMul call is sent to, on the CPU: the host side of the
+library compiled into small programs of its own, no kernel launched."""
+
+import os
+import subprocess
+
+import pytest
+
+from paper_1603_04467_amd import build as B
+
+pytestmark = pytest.mark.timeout(600)
+
+# api.cpp against stand-ins of what its fused calls launch. gemm_route answers
+# with the other kernel each time it is asked, as it may when a tuning knob is
+# set on another thread during a call.
+STAND_INS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "include/tfdense.h"
+#include "paper_1603_04467_amd/csrc/kernels.h"
+namespace tfd {
+static int asked, start;
+static int64_t launched_rows, launched_tiles, summed_rows, summed_tiles;
+GemmRoute gemm_route(const GemmDesc&) {
+  return (start + asked++) % 2 ? GemmRoute::kBf16Tiles128 : GemmRoute::kBf16Whole256;
+}
+static int64_t up(int64_t a, int64_t b) { return (a + b - 1) / b; }
+int64_t gemm_bf16_128_tile_rows(const GemmDesc& d) { return up(d.m, 128); }
+int64_t gemm_bf16_128_tiles(const GemmDesc& d) { return up(d.m, 128) * up(d.n, 128); }
+hipError_t launch_gemm_bf16_256(const GemmDesc& d, hipStream_t) {
+  launched_rows = d.m / 256, launched_tiles = launched_rows * (d.n / 256);
+  return hipSuccess;
+}
+hipError_t launch_gemm_bf16_128(const GemmDesc& d, hipStream_t) {
+  launched_rows = up(d.m, 128), launched_tiles = launched_rows * up(d.n, 128);
+  return hipSuccess;
+}
+hipError_t launch_colsum_final(const float*, float*, int64_t chunks, int64_t, hipStream_t) {
+  summed_rows = chunks;
+  return hipSuccess;
+}
+hipError_t launch_loss_final(const double*, int n, double*, hipStream_t) {
+  summed_tiles = n;
+  return hipSuccess;
+}
+size_t reduction_ws_bytes(int64_t, int64_t, bool) { return 1 << 20; }
+size_t loss_ws_bytes(int64_t, bool) { return 1 << 20; }
+}  // namespace tfd
+using namespace tfd;
+int main() {
+  static char mem[16][1 << 20] __attribute__((aligned(256)));
+  void *a = mem[0], *b = mem[1], *c = mem[2], *f = mem[3], *g = mem[4], *ws = mem[5];
+  uint32_t* mask = reinterpret_cast<uint32_t*>(mem[6]);
+  float *bias = reinterpret_cast<float*>(mem[7]), *db = reinterpret_cast<float*>(mem[8]);
+  double* loss = reinterpret_cast<double*>(mem[9]);
+  const int64_t m = 512, n = 512, k = 64;
+  for (start = 0; start < 2; ++start)
+    for (int call = 0; call < 4; ++call) {
+      asked = 0, launched_rows = launched_tiles = summed_rows = summed_tiles = -1;
+      tfd_status st = TFD_EHIP;
+      if (call == 0)
+        st = tfd_matmul_relu_mask(0, 0, m, n, k, a, k, b, n, bias, c, n, mask, TFD_BF16, TFD_ROUND_NEAREST_EVEN, 0);
+      if (call == 1)
+        st = tfd_matmul_relu_grad_bias_add_grad(0, 0, m, n, k, a, k, b, n, f, c, db, TFD_BF16,
+                                                TFD_ROUND_NEAREST_EVEN, ws, sizeof mem[5], 0);
+      if (call == 2)
+        st = tfd_matmul_relu_mask_grad_bias_add_grad(0, 0, m, n, k, a, k, b, n, mask, c, db, TFD_BF16,
+                                                     TFD_ROUND_NEAREST_EVEN, ws, sizeof mem[5], 0);
+      if (call == 3)
+        st = tfd_matmul_l2_loss_grad(0, 0, m, n, k, a, k, b, n, bias, c, f, g, loss, db, TFD_BF16,
+                                     TFD_ROUND_NEAREST_EVEN, ws, sizeof mem[5], 0);
+      if (call == 0) summed_rows = launched_rows;
+      if (call != 3) summed_tiles = launched_tiles;
+      printf("call %d start %d status %d asked %d rows %lld %lld tiles %lld %lld\n", call, start, (int)st, asked,
+             (long long)launched_rows, (long long)summed_rows, (long long)launched_tiles, (long long)summed_tiles);
+    }
+}
+"""
+
+
+def _build(tmp, source, objects, *flags):
+    src, exe = os.path.join(tmp, "main.cpp"), os.path.join(tmp, "main")
+    with open(src, "w") as f:
+        f.write(source)
+    cmd = [B._hipcc(), "-O1", "-std=c++17", "-I", B.ROOT, src, *objects, *flags, "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return exe
+
+
+def test_fused_calls_decide_their_kernel_once(tmp_path):
+    exe = _build(tmp_path, STAND_INS, [os.path.join(B.CSRC, "api.cpp")], "-Wl,--unresolved-symbols=ignore-all")
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stderr
+    lines = out.stdout.splitlines()
+    assert len(lines) == 8
+    for line in lines:
+        w = line.split()
+        assert w[5] == "0" and int(w[9]) > 0, line              # launched, through a fused kernel
+        assert w[9] == w[10] and w[12] == w[13], line           # sums and partials of the kernel that ran
+        assert w[7] == "1", line
