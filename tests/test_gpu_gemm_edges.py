@@ -94,6 +94,56 @@ def test_f32_values_outside_the_split(tile, layout):
     assert ok[250, :70].all() and np.any(got[250, :70] != 0)
 
 
+@pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
+@pytest.mark.parametrize("tile", [0, *TILES])
+def test_f32_small_operands_beside_large_ones(tile, layout):
+    """Values below 2^-109, whose low bits (below 2^-140: all of them) no 16-bit plane holds, in outputs of ordinary
+    size: beside factors of 2^19 to 2^100, in either operand and in the last, broken k-tile. Each output keeps the
+    fp32 product's bound, and NaN stays in its row."""
+    m, n, k = 300, 280, 70
+    for small_in_a in (True, False):
+        rng = np.random.default_rng([tile, small_in_a])
+        small = rng.standard_normal((m, k)).astype(np.float32)
+        large = rng.standard_normal((k, n)).astype(np.float32)
+        small[3] *= np.float32(2.0 ** -120)
+        small[140] *= np.float32(2.0 ** -126)
+        small[299] *= np.float32(2.0 ** -140)
+        small[200, :] = 0.0
+        small[200, 69] = np.float32(2.0 ** -140)   # one value alone, and its sum with 2^19 exactly 0 in the planes
+        small[17, 4] = np.nan
+        large[:, 5] *= np.float32(2.0 ** 60)
+        large[:, 130] *= np.float32(2.0 ** 100)
+        large[:, 279] = np.float32(2.0 ** 19) * np.where(large[:, 279] > 0, np.float32(1.5), np.float32(1.0))
+        a, b = (small, large) if small_in_a else (large.T.copy(), small.T.copy())
+        ad = torch.from_numpy(a.T.copy() if layout == "TN" else a).to(DEV)
+        bd = torch.from_numpy(b.T.copy() if layout == "NT" else b).to(DEV)
+        c = torch.full((a.shape[0], b.shape[1]), 7.0, device=DEV)
+        with T.tuning(gemm_tile=tile):
+            T.tfd_matmul(ad, bd, c, transpose_a=layout == "TN", transpose_b=layout == "NT")
+        got = c.cpu().numpy().astype(np.float64)
+        a64, b64 = a.astype(np.float64), b.astype(np.float64)
+        want, terms = a64 @ b64, np.abs(a64) @ np.abs(b64)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        ok = np.isfinite(want) & (terms > 2.0 ** -122)   # below, fp32 products are subnormal themselves
+        view = ok if small_in_a else ok.T
+        assert view[[3, 140, 299], 130].all() and view[[3, 140, 299, 200], 279].all() and view[3, 5]
+        bound = product_bound(np.where(ok, terms, 0.0), k, np.where(ok, got, 0.0), "f32")
+        assert np.all(np.abs(np.where(ok, got - want, 0.0)) <= bound)
+
+
+@pytest.mark.parametrize("tile", [0, *TILES])
+def test_f32_largest_omitted_products(tile):
+    """Operands whose omitted plane products are as large as they get (0.97 * 2^-24 of x y, of one sign)."""
+    x = np.float32(1.0 + 2.0 ** -8 - 2.0 ** -17 - 2.0 ** -23)
+    for k in (1, 16, 300):
+        a, b = torch.full((130, k), float(x), device=DEV), torch.full((k, 70), float(x), device=DEV)
+        c = torch.empty(130, 70, device=DEV)
+        with T.tuning(gemm_tile=tile):
+            T.tfd_matmul(a, b, c)
+        got, want = to_f64(c), np.full((130, 70), k * float(x) ** 2)
+        assert np.all(np.abs(got - want) <= product_bound(want, k, got, "f32")), k
+
+
 def test_operands_at_the_end_of_an_allocation():
     """An operand whose last row ends where its storage ends, m/n-contiguous with broken units: the last k-tile is the
     one loaded element by element, and only elements of the operand are read (a value past it would change integers)."""
