@@ -84,13 +84,13 @@ hipError_t launch_layout(const SmallParams& p, int waves, bool vec, unsigned gri
   return launch_w<TA, TB, 4>(p, vec, grid, s);
 }
 
-}  // namespace
-
 // 16-byte loads of the k-contiguous operands need 16-byte aligned rows.
-bool gemm_small_vector_ok(const GemmDesc& d) {
+bool vector_ok(const GemmDesc& d) {
   auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   return (d.ta || (al(d.a) && d.lda % 4 == 0)) && (!d.tb || (al(d.b) && d.ldb % 4 == 0));
 }
+
+}  // namespace
 
 hipError_t launch_gemm_small_f32(const GemmDesc& d, hipStream_t s) {
   SmallParams p;
@@ -115,7 +115,7 @@ hipError_t launch_gemm_small_f32(const GemmDesc& d, hipStream_t s) {
   const int64_t per = (d.k + waves - 1) / waves;
   p.kper = (int)(((per + 7) / 8) * 8);
   if (p.kper == 0) p.kper = 8;
-  const bool vec = gemm_small_vector_ok(d);
+  const bool vec = vector_ok(d);
   const unsigned grid = (unsigned)tiles;
   if (!d.ta && !d.tb) return launch_layout<false, false>(p, waves, vec, grid, s);
   if (!d.ta && d.tb) return launch_layout<false, true>(p, waves, vec, grid, s);

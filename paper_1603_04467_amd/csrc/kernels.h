@@ -84,9 +84,7 @@ int gemm_bf16_256_splits(const GemmDesc& d, int cus);
 // c = epilogue(sum of the `splits` fp32 partials in ws, in order), rounded once (d: the
 // original problem: c, ldc, out type, bias, epi).
 hipError_t launch_splitk_reduce(const float* ws, int splits, const GemmDesc& d, hipStream_t s);
-// Small fp32 problems (gemm_small.hip), and whether their k-contiguous
-// operands allow 16-byte loads.
-bool gemm_small_vector_ok(const GemmDesc& d);
+// Small fp32 problems (gemm_small.hip).
 hipError_t launch_gemm_small_f32(const GemmDesc& d, hipStream_t s);
 
 hipError_t launch_bias_add(const void* value, const float* bias, void* out, int64_t rows, int64_t cols,

@@ -78,18 +78,27 @@ int main() {
 """
 
 
-def _build(tmp, source, objects, *flags):
-    src, exe = os.path.join(tmp, "main.cpp"), os.path.join(tmp, "main")
+def _build(tmp, source, objects):
+    """A program of `source` and compiled objects; what it never calls stays unresolved."""
+    src, obj, exe = (os.path.join(tmp, "main" + e) for e in (".cpp", ".o", ""))
     with open(src, "w") as f:
         f.write(source)
-    cmd = [B._hipcc(), "-O1", "-std=c++17", "-I", B.ROOT, src, *objects, *flags, "-o", exe]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
+    for cmd in ([B._hipcc(), "-O1", "-std=c++17", "-I", B.ROOT, "-c", src, "-o", obj],
+                [B._hipcc(), obj, *objects, "-Wl,--unresolved-symbols=ignore-all", "-o", exe]):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
     return exe
 
 
+def _object(name):
+    path = os.path.join(B.OBJ, name)
+    if not os.path.exists(path):
+        B.build()
+    return path
+
+
 def test_fused_calls_decide_their_kernel_once(tmp_path):
-    exe = _build(tmp_path, STAND_INS, [os.path.join(B.CSRC, "api.cpp")], "-Wl,--unresolved-symbols=ignore-all")
+    exe = _build(tmp_path, STAND_INS, [_object("api.o")])
     out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stderr
     lines = out.stdout.splitlines()
@@ -99,3 +108,49 @@ def test_fused_calls_decide_their_kernel_once(tmp_path):
         assert w[5] == "0" and int(w[9]) > 0, line              # launched, through a fused kernel
         assert w[9] == w[10] and w[12] == w[13], line           # sums and partials of the kernel that ran
         assert w[7] == "1", line
+
+
+# gemm.hip as it is built, with a stand-in for the small-problem kernel; the
+# launch of any other fails without a GPU
+SMALL_STAND_IN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "paper_1603_04467_amd/csrc/kernels.h"
+namespace tfd {
+static bool small;
+hipError_t launch_gemm_small_f32(const GemmDesc&, hipStream_t) {
+  small = true;
+  return hipSuccess;
+}
+int tuning(TuneKnob) { return 0; }
+}  // namespace tfd
+int main(int argc, char** argv) {
+  for (int i = 1; i + 5 < argc; i += 6) {
+    tfd::GemmDesc d = {};
+    d.ta = argv[i][0] == 'T', d.tb = argv[i][1] == 'T';
+    d.m = atoll(argv[i + 1]), d.n = atoll(argv[i + 2]), d.k = atoll(argv[i + 3]);
+    d.lda = (d.ta ? d.m : d.k) + atoll(argv[i + 4]), d.ldb = (d.tb ? d.k : d.n) + atoll(argv[i + 4]), d.ldc = d.n;
+    const uintptr_t at = 4096 + 4 * (uintptr_t)atoll(argv[i + 5]);
+    d.a = reinterpret_cast<const void*>(at), d.b = reinterpret_cast<const void*>(at), d.c = reinterpret_cast<void*>(4096);
+    tfd::small = false;
+    (void)tfd::launch_gemm(d, nullptr);
+    puts(tfd::small ? "small" : "tiles");
+  }
+}
+"""
+
+# Far from the break-even. The small kernel's: single tiles, few columns, rows
+# shorter than a unit, rows that start anywhere; the tile kernels': enough tiles
+# of any size, k over 64 x 64 tiles' wave groups.
+SMALL = ["NN 1 49 100 0 0", "NN 143 2 1267 0 0", "NT 57 6 6231 1 1", "NT 2426 1 1702 0 0", "TN 1 262 144 1 0",
+         "NN 8 160 104 0 0", "TN 6992 24 56 0 0", "NT 200 25 2 1 0", "NN 8 8 3216 1 0", "TN 128 2048 3456 0 1",
+         "NN 100 100 784 0 0"]
+TILES = ["NN 1000 1000 1000 0 0", "NT 8192 4096 4096 0 0", "TN 1024 784 1000 0 0", "NN 300 1024 784 1 1",
+         "NT 2368 4096 64 0 0", "TN 4096 4096 33 0 0"]
+
+
+def test_small_fp32_problems_take_the_small_kernel(tmp_path):
+    exe = _build(tmp_path, SMALL_STAND_IN, [_object("gemm.o")])
+    out = subprocess.run([exe, *" ".join(SMALL + TILES).split()], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stderr
+    assert dict(zip(SMALL + TILES, out.stdout.split())) == {**{s: "small" for s in SMALL}, **{t: "tiles" for t in TILES}}
