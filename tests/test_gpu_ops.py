@@ -353,6 +353,20 @@ def test_l2_loss_grad(dt, count, with_target):
     assert abs(loss.item() - l_want) <= 1e-6 * l_want
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("chunks", [1, 4, 5, 8, 9, 16, 17, 39, 40, 41, 264, 265, 300])
+def test_bias_add_grad_every_chunk_once(dt, chunks):
+    """Column sums of small integers, exact in any order, at the limits of the row-chunk counts (16 rows each) that the
+    final sum's kernels take: up to 4, up to 16, eight groups of whole and broken batches, long runs."""
+    for cols in (1, 31, 33, 300):
+        rng = np.random.default_rng([chunks, cols])
+        x = rng.integers(-8, 9, size=(16 * chunks, cols)).astype(np.float32)
+        g = torch.from_numpy(x).to(DEV, torch.bfloat16 if dt == "bf16" else torch.float32)
+        db = torch.full((cols,), float("nan"), device=DEV)
+        T.tfd_bias_add_grad(g, db)
+        assert_bits(to_f64(db), x.astype(np.float64).sum(0), f"{chunks} chunks {cols} columns")
+
+
 # ---------------------------------------------------------------- reductions
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
