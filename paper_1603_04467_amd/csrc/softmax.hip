@@ -205,13 +205,18 @@ hipError_t launch_row(const T* z, const int32_t* labels, T* grad, double* partia
   return hipGetLastError();
 }
 
+// The fewest threads whose registers hold a row (8 chunks each at most).
+template <typename T>
+int row_threads(int64_t cols) { return cols / elem_traits<T>::vec <= 2048 ? 256 : 1024; }
+
 // Whether rows go one to a block: longer than a wavefront's share, short
-// enough for a block's registers (8 chunks per thread of 1024 threads), and
-// logits and gradient with the same alignment so that both move in whole chunks.
+// enough for a block's registers (8 chunks per thread of 1024 threads), no more
+// than a grid of 2^32 threads holds, and logits and gradient with the same
+// alignment so that both move in whole chunks.
 template <typename T>
 bool row_per_block(const T* z, const T* grad, int64_t rows, int64_t cols) {
   constexpr int V = elem_traits<T>::vec;
-  return cols > kWaveCols && cols / V + 1 <= 8 * 1024 && rows <= 0x7fffffff &&
+  return cols > kWaveCols && cols / V + 1 <= 8 * 1024 && rows * row_threads<T>(cols) < (1LL << 32) &&
          ((reinterpret_cast<uintptr_t>(z) ^ reinterpret_cast<uintptr_t>(grad)) & 15) == 0 &&
          (reinterpret_cast<uintptr_t>(z) & (sizeof(T) - 1)) == 0;
 }
@@ -220,13 +225,13 @@ template <typename T>
 hipError_t launch_rows(const T* z, const int32_t* labels, T* grad, double* partial, int64_t rows, int64_t cols,
                        hipStream_t s) {
   const int64_t chunks = cols / elem_traits<T>::vec;  // at most this many whole ones in a row
-  // the fewest threads whose registers hold the row (8 chunks each at most)
+  if (row_threads<T>(cols) == 1024)
+    return chunks <= 4096 ? launch_row<T, 1024, 4>(z, labels, grad, partial, rows, cols, s)
+                          : launch_row<T, 1024, 8>(z, labels, grad, partial, rows, cols, s);
   if (chunks <= 256) return launch_row<T, 256, 1>(z, labels, grad, partial, rows, cols, s);
   if (chunks <= 512) return launch_row<T, 256, 2>(z, labels, grad, partial, rows, cols, s);
   if (chunks <= 1024) return launch_row<T, 256, 4>(z, labels, grad, partial, rows, cols, s);
-  if (chunks <= 2048) return launch_row<T, 256, 8>(z, labels, grad, partial, rows, cols, s);
-  if (chunks <= 4096) return launch_row<T, 1024, 4>(z, labels, grad, partial, rows, cols, s);
-  return launch_row<T, 1024, 8>(z, labels, grad, partial, rows, cols, s);
+  return launch_row<T, 256, 8>(z, labels, grad, partial, rows, cols, s);
 }
 
 __global__ __launch_bounds__(kThreads) void sum_partials_kernel(const double* partial, int64_t n, double* out) {

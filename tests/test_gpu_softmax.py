@@ -163,3 +163,24 @@ def test_softmax_xent_row_per_block(dt, cols, shift):
         assert np.all(err <= allowed), float(err.max())
         lse = np.log(np.sum(np.exp(z_h - z_h.max(axis=1, keepdims=True)), axis=1))
         assert abs(loss.item() - l_want) <= float(np.sum(K + 4 * np.abs(lse) + 4)) * 2.0 ** -24
+
+
+def test_softmax_xent_more_rows_than_a_grid_of_row_blocks():
+    """2^24 + 3 rows of 520 16-bit columns: a block per row would need more than 2^32 threads."""
+    rows, cols = 2 ** 24 + 3, 520
+    z = torch.zeros(rows, cols, dtype=torch.bfloat16, device=DEV)
+    z[::4096, 7] = 4.0
+    y = (torch.arange(rows, device=DEV) % cols).to(torch.int32)
+    g = torch.full((rows, cols), float("nan"), dtype=torch.bfloat16, device=DEV)
+    loss = torch.full((1,), float("nan"), dtype=torch.float64, device=DEV)
+    T.tfd_softmax_cross_entropy_grad(z, y, g, loss)
+    at = [0, 1, 4096, 2 ** 23 + 5, 2 ** 24 - 1, 2 ** 24, 2 ** 24 + 2]
+    z_h = to_f64(z[at])
+    want, _ = oracle.softmax_cross_entropy_grad(z_h, y[at].cpu().numpy(), grad_dtype="f64")
+    assert np.all(np.abs(to_f64(g[at]) - want) <= 2.0 ** -8 * np.abs(want) + 2.0 ** -22)
+    part = g.view(-1)[::997]  # of every second row
+    assert not (part != part).any()
+    peaked = (rows + 4095) // 4096
+    hit = int(((torch.arange(0, rows, 4096, device=DEV) % cols) == 7).sum())
+    want_loss = (rows - peaked) * np.log(cols) + peaked * np.log(cols - 1 + np.exp(4.0)) - 4.0 * hit
+    assert abs(loss.item() - want_loss) <= 1e-6 * want_loss
