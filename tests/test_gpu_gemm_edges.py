@@ -214,6 +214,30 @@ def test_empty_sum(din, dout, layout, tile):
             assert ((db - want_db).abs() <= 2 * m * 2.0 ** -24 * want_grad.double().abs().sum(0)).all(), (m, n)
 
 
+@pytest.mark.parametrize("tile", [0, *TILES, 8])
+@pytest.mark.parametrize("din,dout", [("f32", "f32"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("side", ["m", "n"])
+def test_more_tiles_than_a_grid_of_their_threads(side, din, dout, tile):
+    """2^30 rows or columns: one workgroup per tile would need 2^32 threads or more on the smaller tiles."""
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    long = 2 ** 30
+    x = torch.arange(512, device=DEV, dtype=torch.float32).to(tdt[din]).repeat(long // 512).view(long, 1)  # exact
+    two, bias = torch.full((1, 1), 2.0, dtype=tdt[din], device=DEV), None
+    c = torch.full((long, 1) if side == "m" else (1, long), float("nan"), dtype=tdt[dout], device=DEV)
+    with T.tuning(gemm_tile=tile):
+        if side == "m":
+            T.tfd_matmul(x, two, c, transpose_b=True)
+        else:
+            bias = torch.arange(2 ** 20, device=DEV, dtype=torch.float32).remainder_(2).repeat(long // 2 ** 20)
+            T.tfd_matmul(two, x.view(1, long), c, bias=bias, epilogue="bias")
+    for part in range(0, long, 2 ** 28):
+        cut = slice(part, part + 2 ** 28)
+        want = 2.0 * x.view(-1)[cut].float()
+        if bias is not None:
+            want += bias[cut]
+        assert torch.equal(c.view(-1)[cut], want.to(tdt[dout])), part
+
+
 # gemm_bf16_128.hip takes whole 16-byte units: one of them; one unit below, at
 # and above a tile edge and a k-tile, fewer k-tiles than stages; with two stages
 # (more than 256 tiles); 256 x 128 tiles (10 k-tiles, more than 256 square ones)
