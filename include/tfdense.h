@@ -346,7 +346,8 @@ TFD_API tfd_status tfd_matmul_l2_loss_grad(int transpose_a, int transpose_b, int
                                    float* bias_grad, tfd_dtype type, tfd_rounding rounding,
                                    void* workspace, size_t workspace_bytes, void* stream);
 
-/* Workspace bytes that tfd_softmax_cross_entropy_grad needs for `rows` rows. */
+/* Workspace bytes that tfd_softmax_cross_entropy_grad needs for `rows` rows.
+ * With 8 bytes per row it is faster on few rows of more than 512 columns. */
 TFD_API size_t tfd_softmax_xent_workspace_size(int64_t rows);
 
 /*

@@ -820,8 +820,13 @@ tfd_status tfd_softmax_cross_entropy_grad(const void* logits, const int32_t* lab
       overlaps(grad, bytes, workspace, need) || overlaps(loss, 8, workspace, need) ||
       overlaps(loss, 8, labels, lbytes) || overlaps(loss, 8, logits, bytes))
     return fail(TFD_EINVAL, "tfd_softmax_cross_entropy_grad: overlapping buffers");
+  // a partial for each row only where all of that workspace is free
+  const size_t full = (size_t)rows * sizeof(double);
+  const bool all = workspace_bytes >= full && !overlaps(grad, bytes, workspace, full) &&
+                   !overlaps(logits, bytes, workspace, full) && !overlaps(labels, lbytes, workspace, full) &&
+                   !overlaps(loss, 8, workspace, full);
   return hip_status(tfd::launch_softmax_xent(logits, labels, grad, loss, rows, cols, type == TFD_BF16, workspace,
-                                             as_stream(stream)),
+                                             all ? full : need, as_stream(stream)),
                     "tfd_softmax_cross_entropy_grad launch");
 }
 

@@ -150,9 +150,11 @@ hipError_t launch_loss_final(const double* partial, int n, double* loss, hipStre
 // Sums `chunks` row-chunk partials of each column, in a fixed order (reduce.hip).
 hipError_t launch_colsum_final(const float* partial, float* db, int64_t chunks, int64_t cols, hipStream_t s);
 
+// ws: softmax_xent_ws_bytes at least; with a float64 per row, long rows go one to
+// a block and not four.
 size_t softmax_xent_ws_bytes(int64_t rows);
 hipError_t launch_softmax_xent(const void* logits, const int32_t* labels, void* grad, double* loss, int64_t rows,
-                               int64_t cols, bool bf16, void* ws, hipStream_t s);
+                               int64_t cols, bool bf16, void* ws, size_t ws_bytes, hipStream_t s);
 
 hipError_t launch_sgd(float* var, float alpha, const float* delta, int64_t count, uint16_t* shadow, bool trunc,
                       hipStream_t s);

@@ -117,7 +117,8 @@ __device__ __forceinline__ float block_reduce(float v, float* sh) {
   return t;
 }
 
-// One row per block of NT threads, up to NT * NC whole 16-byte chunks. Bound
+// One row per block of NT threads (`per_block` rows in turn where the workspace
+// has no partial for each), up to NT * NC whole 16-byte chunks. Bound
 // by HBM (the row in, the gradient out) once the row is read once: 2048 x
 // 32768 bf16 took 487 us with a wavefront per row (2-byte loads, the row read
 // three times, two exponentials per element), 65 us here (4 TB/s). A row that does not start on a
@@ -128,80 +129,86 @@ template <typename T, int NT, int NC>
 __global__ __launch_bounds__(NT) void softmax_xent_row_kernel(const T* __restrict__ z,
                                                               const int32_t* __restrict__ labels,
                                                               T* __restrict__ grad, double* __restrict__ partial,
-                                                              int64_t cols) {
+                                                              int64_t rows, int64_t cols, int per_block) {
   constexpr int V = elem_traits<T>::vec;
   __shared__ float sh[2][NT / kWave];
   const int tid = threadIdx.x;
-  const int64_t row = blockIdx.x;
-  const T* zr = z + row * cols;
-  T* gr = grad + row * cols;
-  const int n = (int)cols;
-  const int head = min(n, (int)((16 - (reinterpret_cast<uintptr_t>(zr) & 15)) & 15) / (int)sizeof(T));
-  const int body = (n - head) / V;  // whole chunks
-  const int tail0 = head + body * V;
-  // the element outside the whole chunks that this thread holds, if any
-  const int edge = tid < head ? tid : (tid - head < n - tail0 ? tail0 + tid - head : -1);
+  double term = 0.0;
+  const int64_t first = (int64_t)blockIdx.x * per_block, end = min(rows, first + per_block);
+  // (the rows' turns need no barrier between them: a wave is at most one
+  // reduction ahead, in the other buffer)
+  for (int64_t row = first; row < end; ++row) {
+    const T* zr = z + row * cols;
+    T* gr = grad + row * cols;
+    const int n = (int)cols;
+    const int head = min(n, (int)((16 - (reinterpret_cast<uintptr_t>(zr) & 15)) & 15) / (int)sizeof(T));
+    const int body = (n - head) / V;  // whole chunks
+    const int tail0 = head + body * V;
+    // the element outside the whole chunks that this thread holds, if any
+    const int edge = tid < head ? tid : (tid - head < n - tail0 ? tail0 + tid - head : -1);
 
-  // Chunks past the row hold -infinity: they leave the maximum as it is and
-  // add exp(-inf) = 0 to the sum.
-  float x[NC][V];
+    // Chunks past the row hold -infinity: they leave the maximum as it is and
+    // add exp(-inf) = 0 to the sum.
+    float x[NC][V];
 #pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    const int c = tid + i * NT;
-    if (c < body) {
-      unpack16<T>(*reinterpret_cast<const u32x4*>(zr + head + (int64_t)c * V), x[i]);
-    } else {
+    for (int i = 0; i < NC; ++i) {
+      const int c = tid + i * NT;
+      if (c < body) {
+        unpack16<T>(*reinterpret_cast<const u32x4*>(zr + head + (int64_t)c * V), x[i]);
+      } else {
 #pragma unroll
-      for (int e = 0; e < V; ++e) x[i][e] = -INFINITY;
+        for (int e = 0; e < V; ++e) x[i][e] = -INFINITY;
+      }
     }
-  }
-  const float ze = edge >= 0 ? load_f32(zr + edge) : -INFINITY;
-  const int32_t y = labels[row];
-  float m = ze;
+    const float ze = edge >= 0 ? load_f32(zr + edge) : -INFINITY;
+    const int32_t y = labels[row];
+    float m = ze;
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
+    for (int i = 0; i < NC; ++i)
 #pragma unroll
-    for (int e = 0; e < V; ++e) m = fmaxf(m, x[i][e]);
-  m = block_reduce<NT, true>(m, sh[0]);
-  const float ee = expf(ze - m);
-  float s = ee;
+      for (int e = 0; e < V; ++e) m = fmaxf(m, x[i][e]);
+    m = block_reduce<NT, true>(m, sh[0]);
+    const float ee = expf(ze - m);
+    float s = ee;
 #pragma unroll
-  for (int i = 0; i < NC; ++i) {
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      x[i][e] = expf(x[i][e] - m);
-      s += x[i][e];
-    }
-  }
-  s = block_reduce<NT, false>(s, sh[1]);
-  const float inv = 1.0f / s;
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    const int c = tid + i * NT;
-    if (c < body) {
-      const int at = head + c * V;
+    for (int i = 0; i < NC; ++i) {
 #pragma unroll
       for (int e = 0; e < V; ++e) {
-        x[i][e] *= inv;
-        if (at + e == y) x[i][e] -= 1.0f;
+        x[i][e] = expf(x[i][e] - m);
+        s += x[i][e];
       }
-      *reinterpret_cast<u32x4*>(gr + head + (int64_t)c * V) = pack16<T>(x[i]);
     }
+    s = block_reduce<NT, false>(s, sh[1]);
+    const float inv = 1.0f / s;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int c = tid + i * NT;
+      if (c < body) {
+        const int at = head + c * V;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          x[i][e] *= inv;
+          if (at + e == y) x[i][e] -= 1.0f;
+        }
+        *reinterpret_cast<u32x4*>(gr + head + (int64_t)c * V) = pack16<T>(x[i]);
+      }
+    }
+    if (edge >= 0) {
+      float p = ee * inv;
+      if (edge == y) p -= 1.0f;
+      store_from_f32(gr + edge, p);
+    }
+    if (tid == 0)
+      term += (y >= 0 && y < n) ? (double)logf(s) + (double)m - (double)load_f32(zr + y) : __builtin_nan("");
   }
-  if (edge >= 0) {
-    float p = ee * inv;
-    if (edge == y) p -= 1.0f;
-    store_from_f32(gr + edge, p);
-  }
-  if (tid == 0)
-    partial[row] = (y >= 0 && y < n) ? (double)logf(s) + (double)m - (double)load_f32(zr + y) : __builtin_nan("");
+  if (tid == 0) partial[blockIdx.x] = term;
 }
 
 template <typename T, int NT, int NC>
 hipError_t launch_row(const T* z, const int32_t* labels, T* grad, double* partial, int64_t rows, int64_t cols,
-                      hipStream_t s) {
-  hipLaunchKernelGGL((softmax_xent_row_kernel<T, NT, NC>), dim3((unsigned)rows), NT, 0, s, z, labels, grad, partial,
-                     cols);
+                      int per_block, hipStream_t s) {
+  hipLaunchKernelGGL((softmax_xent_row_kernel<T, NT, NC>), dim3((unsigned)((rows + per_block - 1) / per_block)), NT, 0,
+                     s, z, labels, grad, partial, rows, cols, per_block);
   return hipGetLastError();
 }
 
@@ -223,15 +230,15 @@ bool row_per_block(const T* z, const T* grad, int64_t rows, int64_t cols) {
 
 template <typename T>
 hipError_t launch_rows(const T* z, const int32_t* labels, T* grad, double* partial, int64_t rows, int64_t cols,
-                       hipStream_t s) {
+                       int per_block, hipStream_t s) {
   const int64_t chunks = cols / elem_traits<T>::vec;  // at most this many whole ones in a row
   if (row_threads<T>(cols) == 1024)
-    return chunks <= 4096 ? launch_row<T, 1024, 4>(z, labels, grad, partial, rows, cols, s)
-                          : launch_row<T, 1024, 8>(z, labels, grad, partial, rows, cols, s);
-  if (chunks <= 256) return launch_row<T, 256, 1>(z, labels, grad, partial, rows, cols, s);
-  if (chunks <= 512) return launch_row<T, 256, 2>(z, labels, grad, partial, rows, cols, s);
-  if (chunks <= 1024) return launch_row<T, 256, 4>(z, labels, grad, partial, rows, cols, s);
-  return launch_row<T, 256, 8>(z, labels, grad, partial, rows, cols, s);
+    return chunks <= 4096 ? launch_row<T, 1024, 4>(z, labels, grad, partial, rows, cols, per_block, s)
+                          : launch_row<T, 1024, 8>(z, labels, grad, partial, rows, cols, per_block, s);
+  if (chunks <= 256) return launch_row<T, 256, 1>(z, labels, grad, partial, rows, cols, per_block, s);
+  if (chunks <= 512) return launch_row<T, 256, 2>(z, labels, grad, partial, rows, cols, per_block, s);
+  if (chunks <= 1024) return launch_row<T, 256, 4>(z, labels, grad, partial, rows, cols, per_block, s);
+  return launch_row<T, 256, 8>(z, labels, grad, partial, rows, cols, per_block, s);
 }
 
 __global__ __launch_bounds__(kThreads) void sum_partials_kernel(const double* partial, int64_t n, double* out) {
@@ -250,15 +257,17 @@ __global__ __launch_bounds__(kThreads) void sum_partials_kernel(const double* pa
 
 }  // namespace
 
-// One partial per row at most (a block per row).
-size_t softmax_xent_ws_bytes(int64_t rows) { return (size_t)(rows > 0 ? rows : 1) * sizeof(double); }
+// One partial per block of four rows.
+size_t softmax_xent_ws_bytes(int64_t rows) {
+  return (size_t)(rows > 0 ? (rows + kRowsPerBlock - 1) / kRowsPerBlock : 1) * sizeof(double);
+}
 
 template <typename T>
 static hipError_t launch_t(const T* logits, const int32_t* labels, T* grad, double* partial, int64_t rows,
-                           int64_t cols, int64_t* blocks, hipStream_t s) {
+                           int64_t cols, int per_block, int64_t* blocks, hipStream_t s) {
   if (row_per_block(logits, grad, rows, cols)) {
-    *blocks = rows;
-    return launch_rows(logits, labels, grad, partial, rows, cols, s);
+    *blocks = (rows + per_block - 1) / per_block;
+    return launch_rows(logits, labels, grad, partial, rows, cols, per_block, s);
   }
   *blocks = (rows + kRowsPerBlock - 1) / kRowsPerBlock;
   hipLaunchKernelGGL((softmax_xent_kernel<T>), dim3((unsigned)*blocks), kThreads, 0, s, logits, labels, grad, partial,
@@ -267,12 +276,14 @@ static hipError_t launch_t(const T* logits, const int32_t* labels, T* grad, doub
 }
 
 hipError_t launch_softmax_xent(const void* logits, const int32_t* labels, void* grad, double* loss, int64_t rows,
-                               int64_t cols, bool bf16_t, void* ws, hipStream_t s) {
+                               int64_t cols, bool bf16_t, void* ws, size_t ws_bytes, hipStream_t s) {
   double* partial = static_cast<double*>(ws);
+  const int per_block = ws_bytes >= (size_t)rows * sizeof(double) ? 1 : kRowsPerBlock;
   int64_t blocks = 0;
   if (rows > 0) {
-    const hipError_t e = bf16_t ? launch_t((const bf16*)logits, labels, (bf16*)grad, partial, rows, cols, &blocks, s)
-                                : launch_t((const float*)logits, labels, (float*)grad, partial, rows, cols, &blocks, s);
+    const hipError_t e =
+        bf16_t ? launch_t((const bf16*)logits, labels, (bf16*)grad, partial, rows, cols, per_block, &blocks, s)
+               : launch_t((const float*)logits, labels, (float*)grad, partial, rows, cols, per_block, &blocks, s);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(sum_partials_kernel, 1, kThreads, 0, s, (const double*)partial, blocks, loss);

@@ -145,7 +145,7 @@ class DenseStep:
 
         need = [T.tfd_reduction_workspace_size(N, w.dims[l + 1], self.act) for l in range(L)]
         need.append(T.tfd_loss_workspace_size(N * w.dims[-1], self.act))
-        need.append(T.tfd_softmax_xent_workspace_size(N))
+        need.append(max(T.tfd_softmax_xent_workspace_size(N), 8 * N))  # (8 per row: faster on few long rows)
         need += [T.tfd_matmul_relu_grad_workspace_size(N, w.dims[l], self.act) for l in range(1, L)]
         need.append(T.tfd_matmul_l2_loss_grad_workspace_size(N, w.dims[-1], self.act))
         need += [T.tfd_matmul_workspace_size(N, w.dims[l], w.dims[l + 1], self.act, self.act, transpose_b=True)

@@ -485,7 +485,8 @@ def tfd_softmax_cross_entropy_grad(logits, labels, grad, loss, workspace=None, s
         raise ValueError("labels must be contiguous int32 with one entry per row")
     if loss.dtype != torch.float64 or loss.numel() < 1:
         raise ValueError("loss must be a float64 tensor")
-    ws = _workspace(tfd_softmax_xent_workspace_size(rows), logits.device, workspace)
+    # 8 bytes per row: more than needed, faster on few long rows
+    ws = _workspace(max(tfd_softmax_xent_workspace_size(rows), 8 * rows), logits.device, workspace)
     _check(load().tfd_softmax_cross_entropy_grad(_ptr(logits), _ptr(labels), _ptr(grad), _ptr(loss), rows, cols,
                                                  _dtype(logits), _ptr(ws), ws.numel(), _stream(stream)))
     return grad, loss

@@ -184,3 +184,27 @@ def test_softmax_xent_more_rows_than_a_grid_of_row_blocks():
     hit = int(((torch.arange(0, rows, 4096, device=DEV) % cols) == 7).sum())
     want_loss = (rows - peaked) * np.log(cols) + peaked * np.log(cols - 1 + np.exp(4.0)) - 4.0 * hit
     assert abs(loss.item() - want_loss) <= 1e-6 * want_loss
+
+
+@pytest.mark.parametrize("rows", [1, 4, 5, 11, 600])
+@pytest.mark.parametrize("dt,cols", [("f32", 10), ("f32", 513), ("bf16", 1031), ("bf16", 32768), ("f32", 65551)])
+def test_softmax_xent_workspace_of_8_bytes_per_four_rows(dt, cols, rows):
+    """The workspace that the query asks for, 8 bytes for every four rows, is enough for every kernel, which stays
+    inside it; with 8 bytes per row the gradient is the same."""
+    need = T.tfd_softmax_xent_workspace_size(rows)
+    assert need == 8 * ((rows + 3) // 4)
+    rng = np.random.default_rng([rows, cols])
+    z_h, z = _logits(rng, rows, cols, dt, 4.0)
+    y = rng.integers(0, cols, size=rows, dtype=np.int32)
+    got = []
+    for nbytes in (need, 8 * rows):
+        buf = torch.full((nbytes + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+        g = torch.full_like(z, float("nan"))
+        loss = torch.full((1,), float("nan"), dtype=torch.float64, device=DEV)
+        T.tfd_softmax_cross_entropy_grad(z, torch.from_numpy(y).to(DEV), g, loss, workspace=buf[:nbytes])
+        assert bool((buf[nbytes:] == 0x5A).all())
+        got.append((g, loss.item()))
+    assert torch.equal(got[0][0], got[1][0])
+    _, want = oracle.softmax_cross_entropy_grad(z_h, y, grad_dtype="f64")
+    for _, loss in got:
+        assert abs(loss - want) <= 1e-6 * want
