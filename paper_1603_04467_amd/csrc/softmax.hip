@@ -117,27 +117,29 @@ __device__ __forceinline__ float block_reduce(float v, float* sh) {
   return t;
 }
 
-// One row per block of NT threads (`per_block` rows in turn where the workspace
-// has no partial for each), up to NT * NC whole 16-byte chunks. Bound
-// by HBM (the row in, the gradient out) once the row is read once: 2048 x
-// 32768 bf16 took 487 us with a wavefront per row (2-byte loads, the row read
-// three times, two exponentials per element), 65 us here (4 TB/s). A row that does not start on a
-// 16-byte boundary has up to V - 1 elements before its first whole chunk and
-// after its last, one per thread; logits and gradient rows share their
-// alignment (checked by the launcher).
-template <typename T, int NT, int NC>
+// One row per block of NT threads (kPerBlock rows in turn where the workspace
+// has no partial for each), up to NT * NC whole 16-byte chunks. Bound by HBM
+// (the row in, the gradient out) once the row is read once: 2048 x 32768 bf16
+// took 487 us with a wavefront per row (2-byte loads, the row read three times,
+// two exponentials per element), 65-73 us here (3.7-4.1 TB/s). A row that does
+// not start on a 16-byte boundary has up to V - 1 elements before its first
+// whole chunk and after its last, one per thread; logits and gradient rows
+// share their alignment (checked by the launcher).
+template <typename T, int NT, int NC, int kPerBlock>
 __global__ __launch_bounds__(NT) void softmax_xent_row_kernel(const T* __restrict__ z,
                                                               const int32_t* __restrict__ labels,
                                                               T* __restrict__ grad, double* __restrict__ partial,
-                                                              int64_t rows, int64_t cols, int per_block) {
+                                                              int64_t rows, int64_t cols) {
   constexpr int V = elem_traits<T>::vec;
   __shared__ float sh[2][NT / kWave];
   const int tid = threadIdx.x;
   double term = 0.0;
-  const int64_t first = (int64_t)blockIdx.x * per_block, end = min(rows, first + per_block);
   // (the rows' turns need no barrier between them: a wave is at most one
   // reduction ahead, in the other buffer)
-  for (int64_t row = first; row < end; ++row) {
+#pragma unroll 1
+  for (int r = 0; r < kPerBlock; ++r) {
+    const int64_t row = (int64_t)blockIdx.x * kPerBlock + r;
+    if (kPerBlock > 1 && row >= rows) break;
     const T* zr = z + row * cols;
     T* gr = grad + row * cols;
     const int n = (int)cols;
@@ -207,8 +209,13 @@ __global__ __launch_bounds__(NT) void softmax_xent_row_kernel(const T* __restric
 template <typename T, int NT, int NC>
 hipError_t launch_row(const T* z, const int32_t* labels, T* grad, double* partial, int64_t rows, int64_t cols,
                       int per_block, hipStream_t s) {
-  hipLaunchKernelGGL((softmax_xent_row_kernel<T, NT, NC>), dim3((unsigned)((rows + per_block - 1) / per_block)), NT, 0,
-                     s, z, labels, grad, partial, rows, cols, per_block);
+  if (per_block == 1)
+    hipLaunchKernelGGL((softmax_xent_row_kernel<T, NT, NC, 1>), dim3((unsigned)rows), NT, 0, s, z, labels, grad,
+                       partial, rows, cols);
+  else
+    hipLaunchKernelGGL((softmax_xent_row_kernel<T, NT, NC, kRowsPerBlock>),
+                       dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)), NT, 0, s, z, labels, grad,
+                       partial, rows, cols);
   return hipGetLastError();
 }
 
