@@ -154,3 +154,45 @@ def test_small_fp32_problems_take_the_small_kernel(tmp_path):
     out = subprocess.run([exe, *" ".join(SMALL + TILES).split()], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stderr
     assert dict(zip(SMALL + TILES, out.stdout.split())) == {**{s: "small" for s in SMALL}, **{t: "tiles" for t in TILES}}
+
+
+# the routes of gemm.hip as they are built
+ROUTES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "paper_1603_04467_amd/csrc/kernels.h"
+namespace tfd {
+int tuning(TuneKnob) { return 0; }
+}  // namespace tfd
+int main(int argc, char** argv) {
+  for (int i = 1; i + 3 < argc; i += 4) {
+    tfd::GemmDesc d = {};
+    d.in_bf16 = d.out_bf16 = true;
+    d.ta = argv[i][0] == 'T', d.tb = argv[i][1] == 'T';
+    d.m = atoll(argv[i + 1]), d.n = atoll(argv[i + 2]), d.k = atoll(argv[i + 3]);
+    d.lda = d.ta ? d.m : d.k, d.ldb = d.tb ? d.k : d.n, d.ldc = d.n;
+    d.a = d.b = reinterpret_cast<const void*>(4096), d.c = reinterpret_cast<void*>(4096);
+    const tfd::GemmRoute r = tfd::gemm_route(d);
+    if (r != tfd::GemmRoute::kBf16Tiles128)
+      puts(r == tfd::GemmRoute::kBf16Whole256 ? "whole" : "other");
+    else if (tfd::gemm_bf16_128_tile_rows(d) == (d.m + 255) / 256 && d.m > 128)
+      puts("tall");
+    else
+      puts(tfd::gemm_bf16_128_tiles(d) <= 256 ? "four" : "two");
+  }
+}
+"""
+
+
+def test_16_bit_routes(tmp_path):
+    """Which kernel, and which of its forms (128 x 128 tiles in four or two stages, 256 x 128 tiles), the sizes of
+    the GPU tests of the fused epilogues take, and sizes far to either side of the rules."""
+    exe = _build(tmp_path, ROUTES, [_object(o) for o in ("gemm.o", "gemm_bf16.o", "gemm_bf16_tn.o", "gemm_bf16_128.o")])
+    want = {(1800, 2040, 1000): "four", (3000, 2504, 328): "two", (2176, 2056, 1288): "tall", (2048, 4096, 576): "tall",
+            (16384, 4096, 4096): "whole", (4096, 8192, 512): "whole", (2048, 4096, 4096): "tall",
+            (2048, 2048, 4096): "four", (16000, 1000, 1000): "tall", (256, 1024, 1024): "other", (100, 100, 784): "other",
+            (1000, 1001, 1000): "other"}
+    keys = [(lay, *size) for lay in ("NN", "NT", "TN") for size in want]
+    out = subprocess.run([exe, *[str(v) for k in keys for v in k]], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stderr
+    assert dict(zip(keys, out.stdout.split())) == {k: want[k[1:]] for k in keys}
