@@ -94,41 +94,58 @@ def test_f32_values_outside_the_split(tile, layout):
     assert ok[250, :70].all() and np.any(got[250, :70] != 0)
 
 
+def _small_beside_large(m, n, k, layout, tile, small_in_a):
+    """Values below 2^-109, whose low bits (below 2^-140: all of them) no 16-bit plane holds, in outputs of ordinary
+    size: beside factors of 2^19 to 2^100, in the last k too. Each output keeps the fp32 product's bound, and NaN
+    stays in its row. m rows of small values, n columns of large ones; the product as it is or transposed."""
+    rng = np.random.default_rng([tile, small_in_a, m, n, k])
+    small = rng.standard_normal((m, k)).astype(np.float32)
+    large = rng.standard_normal((k, n)).astype(np.float32)
+    tiny = [3 % m, 140 % m, m - 1]
+    for row, e in zip(tiny, (-120, -126, -140)):
+        small[row] *= np.float32(2.0 ** e)
+    zero, nan = [r for r in range(m) if r not in tiny][:2] if m > 4 else (None, None)
+    if zero is not None:
+        small[zero] = 0.0
+        small[zero, k - 1] = np.float32(2.0 ** -140)  # one value alone, exactly 0 in the planes times 2^19
+        small[nan, 4] = np.nan
+    large[:, 0] *= np.float32(2.0 ** 60)
+    if n > 1:
+        large[:, n // 2] *= np.float32(2.0 ** 100)
+    if n > 2:
+        large[:, n - 1] = np.float32(2.0 ** 19) * np.where(large[:, n - 1] > 0, np.float32(1.5), np.float32(1.0))
+    a, b = (small, large) if small_in_a else (large.T.copy(), small.T.copy())
+    ad = torch.from_numpy(a.T.copy() if layout == "TN" else a).to(DEV)
+    bd = torch.from_numpy(b.T.copy() if layout == "NT" else b).to(DEV)
+    c = torch.full((a.shape[0], b.shape[1]), 7.0, device=DEV)
+    with T.tuning(gemm_tile=tile):
+        T.tfd_matmul(ad, bd, c, transpose_a=layout == "TN", transpose_b=layout == "NT")
+    got = c.cpu().numpy().astype(np.float64)
+    a64, b64 = a.astype(np.float64), b.astype(np.float64)
+    want, terms = a64 @ b64, np.abs(a64) @ np.abs(b64)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    ok = np.isfinite(want) & (terms > 2.0 ** -122)   # below, fp32 products are subnormal themselves
+    view = ok if small_in_a else ok.T
+    assert view[tiny[0], 0] and view[tiny, n // 2].all()
+    if n > 2 and zero is not None:
+        assert view[[*tiny, zero], n - 1].all()
+    bound = product_bound(np.where(ok, terms, 0.0), k, np.where(ok, got, 0.0), "f32")
+    assert np.all(np.abs(np.where(ok, got - want, 0.0)) <= bound)
+
+
 @pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
 @pytest.mark.parametrize("tile", [0, *TILES])
 def test_f32_small_operands_beside_large_ones(tile, layout):
-    """Values below 2^-109, whose low bits (below 2^-140: all of them) no 16-bit plane holds, in outputs of ordinary
-    size: beside factors of 2^19 to 2^100, in either operand and in the last, broken k-tile. Each output keeps the
-    fp32 product's bound, and NaN stays in its row."""
-    m, n, k = 300, 280, 70
-    for small_in_a in (True, False):
-        rng = np.random.default_rng([tile, small_in_a])
-        small = rng.standard_normal((m, k)).astype(np.float32)
-        large = rng.standard_normal((k, n)).astype(np.float32)
-        small[3] *= np.float32(2.0 ** -120)
-        small[140] *= np.float32(2.0 ** -126)
-        small[299] *= np.float32(2.0 ** -140)
-        small[200, :] = 0.0
-        small[200, 69] = np.float32(2.0 ** -140)   # one value alone, and its sum with 2^19 exactly 0 in the planes
-        small[17, 4] = np.nan
-        large[:, 5] *= np.float32(2.0 ** 60)
-        large[:, 130] *= np.float32(2.0 ** 100)
-        large[:, 279] = np.float32(2.0 ** 19) * np.where(large[:, 279] > 0, np.float32(1.5), np.float32(1.0))
-        a, b = (small, large) if small_in_a else (large.T.copy(), small.T.copy())
-        ad = torch.from_numpy(a.T.copy() if layout == "TN" else a).to(DEV)
-        bd = torch.from_numpy(b.T.copy() if layout == "NT" else b).to(DEV)
-        c = torch.full((a.shape[0], b.shape[1]), 7.0, device=DEV)
-        with T.tuning(gemm_tile=tile):
-            T.tfd_matmul(ad, bd, c, transpose_a=layout == "TN", transpose_b=layout == "NT")
-        got = c.cpu().numpy().astype(np.float64)
-        a64, b64 = a.astype(np.float64), b.astype(np.float64)
-        want, terms = a64 @ b64, np.abs(a64) @ np.abs(b64)
-        assert np.array_equal(np.isnan(got), np.isnan(want))
-        ok = np.isfinite(want) & (terms > 2.0 ** -122)   # below, fp32 products are subnormal themselves
-        view = ok if small_in_a else ok.T
-        assert view[[3, 140, 299], 130].all() and view[[3, 140, 299, 200], 279].all() and view[3, 5]
-        bound = product_bound(np.where(ok, terms, 0.0), k, np.where(ok, got, 0.0), "f32")
-        assert np.all(np.abs(np.where(ok, got - want, 0.0)) <= bound)
+    for m, n, k in [(300, 280, 70), (264, 272, 160)]:  # with and without k-tiles and units loaded apart
+        for small_in_a in (True, False):
+            _small_beside_large(m, n, k, layout, tile, small_in_a)
+
+
+@pytest.mark.parametrize("layout", ["NN", "TN"])
+def test_f32_small_operands_in_rows_shorter_than_a_unit(layout):
+    """The kernel that loads every k-tile element by element sums again as the others do."""
+    for k in (5, 70):
+        _small_beside_large(300, 2, k, layout, 4, layout == "NN")  # NN: b is k x 2; TN: a is k x 2
 
 
 @pytest.mark.parametrize("tile", [0, *TILES])
