@@ -147,7 +147,7 @@ struct FusedPlan {
   int64_t rows, tiles;   // tile rows, each with its row of column sums; tiles
 };
 FusedPlan fused_plan(const tfd::GemmDesc& d) {
-  const tfd::GemmRoute r = tfd::gemm_route(d);
+  const tfd::GemmRoute r = tfd::gemm_fused_route(d);
   if (r == tfd::GemmRoute::kBf16Whole256) return {r, d.m / 256, (d.m / 256) * (d.n / 256)};
   if (r == tfd::GemmRoute::kBf16Tiles128) return {r, tfd::gemm_bf16_128_tile_rows(d), tfd::gemm_bf16_128_tiles(d)};
   return {tfd::GemmRoute::kOther, 0, 0};

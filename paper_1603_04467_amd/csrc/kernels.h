@@ -78,6 +78,10 @@ hipError_t launch_gemm_bf16_128(const GemmDesc& d, hipStream_t s);
 // answer.
 enum class GemmRoute { kOther, kBf16Whole256, kBf16Tiles128 };
 GemmRoute gemm_route(const GemmDesc& d);
+// The kernel of a call with a fused epilogue: gemm_route's, or one with the
+// epilogues that sums k in the same order, so that the bits stay the plain
+// call's.
+GemmRoute gemm_fused_route(const GemmDesc& d);
 // Number of k splits worth using for a whole-tile 16-bit problem on `cus`
 // compute units (1: none).
 int gemm_bf16_256_splits(const GemmDesc& d, int cus);

@@ -10,7 +10,7 @@ from paper_1603_04467_amd import build as B
 
 pytestmark = pytest.mark.timeout(600)
 
-# api.cpp against stand-ins of what its fused calls launch. gemm_route answers
+# api.cpp against stand-ins of what its fused calls launch. The route answers
 # with the other kernel each time it is asked, as it may when a tuning knob is
 # set on another thread during a call.
 STAND_INS = r"""
@@ -21,7 +21,7 @@ STAND_INS = r"""
 namespace tfd {
 static int asked, start;
 static int64_t launched_rows, launched_tiles, summed_rows, summed_tiles;
-GemmRoute gemm_route(const GemmDesc&) {
+GemmRoute gemm_fused_route(const GemmDesc&) {
   return (start + asked++) % 2 ? GemmRoute::kBf16Tiles128 : GemmRoute::kBf16Whole256;
 }
 static int64_t up(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -165,14 +165,14 @@ namespace tfd {
 int tuning(TuneKnob) { return 0; }
 }  // namespace tfd
 int main(int argc, char** argv) {
-  for (int i = 1; i + 3 < argc; i += 4) {
+  for (int i = argc % 4 == 2 ? 2 : 1; i + 3 < argc; i += 4) {  // (a word more: fused calls)
     tfd::GemmDesc d = {};
     d.in_bf16 = d.out_bf16 = true;
     d.ta = argv[i][0] == 'T', d.tb = argv[i][1] == 'T';
     d.m = atoll(argv[i + 1]), d.n = atoll(argv[i + 2]), d.k = atoll(argv[i + 3]);
     d.lda = d.ta ? d.m : d.k, d.ldb = d.tb ? d.k : d.n, d.ldc = d.n;
     d.a = d.b = reinterpret_cast<const void*>(4096), d.c = reinterpret_cast<void*>(4096);
-    const tfd::GemmRoute r = tfd::gemm_route(d);
+    const tfd::GemmRoute r = argc % 4 == 2 ? tfd::gemm_fused_route(d) : tfd::gemm_route(d);
     if (r != tfd::GemmRoute::kBf16Tiles128)
       puts(r == tfd::GemmRoute::kBf16Whole256 ? "whole" : "other");
     else if (tfd::gemm_bf16_128_tile_rows(d) == (d.m + 255) / 256 && d.m > 128)
@@ -192,7 +192,13 @@ def test_16_bit_routes(tmp_path):
             (16384, 4096, 4096): "whole", (4096, 8192, 512): "whole", (2048, 4096, 4096): "tall",
             (2048, 2048, 4096): "four", (16000, 1000, 1000): "tall", (256, 1024, 1024): "other", (100, 100, 784): "other",
             (1000, 1001, 1000): "other"}
-    keys = [(lay, *size) for lay in ("NN", "NT", "TN") for size in want]
-    out = subprocess.run([exe, *[str(v) for k in keys for v in k]], capture_output=True, text=True, timeout=60)
-    assert out.returncode == 0, out.stderr
-    assert dict(zip(keys, out.stdout.split())) == {k: want[k[1:]] for k in keys}
+    # fused calls: as the plain ones, but for problems on 64 x 64 tiles and whole k-tiles without wave groups
+    fused = {**want, (2048, 1792, 128): "four", (8448, 768, 128): "two", (1792, 3584, 128): "two",
+             (1000, 1024, 200): "other"}
+    plain = {**want, (2048, 1792, 128): "other", (8448, 768, 128): "other", (1792, 3584, 128): "other",
+             (1000, 1024, 200): "other"}
+    for words, table in (([], plain), (["fused"], fused)):
+        keys = [(lay, *size) for lay in ("NN", "NT", "TN") for size in table]
+        out = subprocess.run([exe, *words, *[str(v) for k in keys for v in k]], capture_output=True, text=True, timeout=60)
+        assert out.returncode == 0, out.stderr
+        assert dict(zip(keys, out.stdout.split())) == {k: table[k[1:]] for k in keys}

@@ -323,3 +323,19 @@ def test_tiles128_fused_epilogues(size, layout):
     T.tfd_l2_loss_grad(want, target, want_grad, want_loss)
     assert torch.equal(out, want) and torch.equal(grad, want_grad) and sums_ok(d, grad)
     assert abs(loss.item() - want_loss.item()) <= m * n * 2.0 ** -52 * want_loss.item()
+
+
+@pytest.mark.parametrize("size", [(2048, 1792, 128), (8448, 768, 128), (1792, 3584, 128), (1800, 1024, 64)])
+@pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
+def test_fused_epilogues_beside_64_wide_plain_tiles(size, layout):
+    """Sizes whose plain call runs on 64 x 64 tiles and whose fused calls on 128 x 128 ones: the same bits."""
+    with T.tuning(gemm_tile=4):
+        m, n, k = size
+        g = torch.Generator(device=DEV).manual_seed(5)
+        a = torch.randn(*((k, m) if layout == "TN" else (m, k)), generator=g, device=DEV).to(torch.bfloat16)
+        b = torch.randn(*((n, k) if layout == "NT" else (k, n)), generator=g, device=DEV).to(torch.bfloat16)
+        kw = dict(transpose_a=layout == "TN", transpose_b=layout == "NT")
+        c64 = T.tfd_matmul(a, b, torch.empty(m, n, dtype=torch.bfloat16, device=DEV), **kw)
+    c = T.tfd_matmul(a, b, torch.empty(m, n, dtype=torch.bfloat16, device=DEV), **kw)
+    assert torch.equal(c, c64)
+    test_tiles128_fused_epilogues(size, layout)
